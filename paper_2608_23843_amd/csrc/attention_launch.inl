@@ -9,75 +9,28 @@ namespace pkv {
 // waves per SIMD), each wave streaming many pages; fewer chunks also keep the
 // final merge short.
 static int attention_sched(const Geo &g, int pages_per_chunk);
-constexpr int64_t kAttnGroups = 256;   // workgroups aimed at, one per CU
 
 // The plan when every sequence has max_T tokens; it sizes the workspace.
 AttnPlan attention_plan(const Geo &g, int64_t max_T) {
     AttnPlan p{};
     const int64_t n_pages = std::max<int64_t>(1, ceil_div(max_T, g.P));
-    const int64_t heads = (int64_t)g.B * g.Hkv;
+    const ChunkPlan c = chunk_plan_equal(g.B, g.Hkv, n_pages);
     p.use_mfma = mfma_supported(g) ? 1 : 0;
-    p.pages_per_chunk = (int)std::max<int64_t>(1, ceil_div(n_pages * heads, kAttnGroups));
-    p.n_chunks = (int)ceil_div(n_pages, p.pages_per_chunk);
+    p.pages_per_chunk = c.pages_per_chunk;
+    p.n_chunks = c.n_chunks;
     p.sched = attention_sched(g, p.pages_per_chunk);
     return p;
 }
 
-// The plan for these lengths. The pages per chunk come from the pages there
-// are, not from the longest sequence times the batch: in a batch of mixed
-// lengths the long heads would otherwise get as few workgroups as the short
-// ones and finish alone (128 heads of 16 sequences of 500 to 16,363 tokens: 91
-// us with two chunks each, 66 us with one to five; 32 sequences of one KV head
-// and up to 32,001 tokens: 43 -> 32 us). A chunk beyond one per CU would start
-// when another ends, so chunks grow until their number is at most 256, or half
-// as many again as heads when there are more heads than that, and fits the
-// partial states of a workspace sized for max_T; and a head is not cut into
-// more than 32 chunks that equal lengths would not give it, since its merge
-// takes a round trip per 32 (8 sequences of one KV head and up to 65,001
-// tokens: 28.6 us with 32, 29.4 us with 79). The grid holds the chunks there
-// are: with workgroups that find nothing to do in it the same plan lost (91 ->
-// 96 us). For equal lengths this is attention_plan.
+// The plan for these lengths (chunk_plan), with the chunks of MixedSeq filled in
+// where the heads have different numbers of them.
 static AttnPlan attention_plan_for(const Geo &g, const AttnPlan &full, const SeqArgs &seq, MixedSeq &out, bool &equal) {
-    equal = std::all_of(seq.len, seq.len + g.B, [&](int32_t n) { return n == seq.len[0]; });
-    if (equal) return full;
-    const int64_t heads = (int64_t)g.B * g.Hkv;
-    const int64_t most = std::min({std::max(kAttnGroups, heads + heads / 2), heads * ((full.n_chunks + 3) / 4 * 4),
-                                   (int64_t)kMaxChunkSlots * g.Hkv});
-    auto pages = [&](int b) { return std::max<int64_t>(1, ceil_div(seq.len[b], g.P)); };
-    int64_t total = 0, longest = 1;
-    for (int b = 0; b < g.B; ++b) {
-        total += pages(b);
-        longest = std::max(longest, pages(b));
-    }
-    int64_t ppc = std::max(ceil_div(total * g.Hkv, kAttnGroups), ceil_div(longest, std::max(32, full.n_chunks)));
-    for (;; ppc += std::max<int64_t>(1, ppc / 32)) {
-        int64_t n = 0;
-        for (int b = 0; b < g.B; ++b) n += ceil_div(pages(b), ppc);
-        if (n * g.Hkv <= most || ppc >= full.pages_per_chunk) break;
-    }
+    const ChunkPlan c = chunk_plan(g.B, g.Hkv, g.P, {full.pages_per_chunk, full.n_chunks, true}, seq.len, out);
+    equal = c.equal;
     AttnPlan p = full;
-    p.pages_per_chunk = (int)std::min<int64_t>(ppc, full.pages_per_chunk);
-    p.n_chunks = (int)ceil_div(longest, p.pages_per_chunk);
-    p.sched = attention_sched(g, p.pages_per_chunk);
-    out.first[0] = 0;
-    equal = true;   // of different lengths, but the same number of chunks
-    for (int b = 0; b < g.B; ++b) {
-        const int n = (int)ceil_div(pages(b), p.pages_per_chunk);
-        out.len[b] = seq.len[b];
-        out.first[b + 1] = out.first[b] + n;
-        if (n != p.n_chunks) equal = false;
-    }
-    if (!equal) {
-        int order[kMaxBatchArgs];
-        for (int b = 0; b < g.B; ++b) order[b] = b;
-        std::sort(order, order + g.B, [&](int x, int y) { return seq.len[x] != seq.len[y] ? seq.len[x] > seq.len[y] : x < y; });
-        int i = 0;
-        for (int x = 0; x < g.B; ++x)
-            for (int c = 0; c < out.first[order[x] + 1] - out.first[order[x]]; ++c, ++i) {
-                out.seq_of[i] = (uint8_t)order[x];
-                out.chunk_of[i] = (uint8_t)c;
-            }
-    }
+    p.pages_per_chunk = c.pages_per_chunk;
+    p.n_chunks = c.n_chunks;
+    p.sched = attention_sched(g, c.pages_per_chunk);
     return p;
 }
 

@@ -6,15 +6,14 @@
 #include <stdint.h>
 
 #include "puzzlekv.h"
+#include "attention_plan.h"
 
 namespace pkv {
 
-constexpr int kMaxBatchArgs = 256;   // sequences whose lengths travel in kernel arguments
 constexpr int kCompressItemsPerLaunch = 96;
 constexpr int kCopyItemsPerLaunch = 64;
 
 __host__ __device__ inline int r4(int r) { return (r + 3) & ~3; }
-__host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Elements of a packed factor page pair at ranks (rk, rv). kt: R_K stored
 // transposed, d x r4(rk) (caches of pre-RoPE keys).
@@ -178,24 +177,6 @@ struct CopyItems {
 struct SeqArgs {
     int32_t n;  // batch
     int32_t len[kMaxBatchArgs];
-};
-// Sequence lengths of an attention launch and its chunks: each KV head of
-// sequence b is split over a number of workgroups, and their partial states
-// follow those of the heads before it. With the same number for every head
-// (EqualSeq) the grid is (chunk, head); otherwise (MixedSeq) the heads of
-// sequence b have first[b + 1] - first[b] chunks and workgroup i * Hkv + h
-// serves chunk chunk_of[i] of head h of sequence seq_of[i], longest sequences
-// first. Two types and not a flag: the lookups cost a 16 us call 0.2 us also
-// where it did not make them.
-constexpr int kMaxChunkSlots = 384;   // chunks of one KV head over all sequences: at most 256, or 1.5 per sequence
-struct EqualSeq {
-    int32_t len[kMaxBatchArgs];
-    int32_t n_chunks;   // read together with the kernel's next argument
-};
-struct MixedSeq {
-    int32_t len[kMaxBatchArgs];
-    int32_t first[kMaxBatchArgs + 1];
-    uint8_t seq_of[kMaxChunkSlots], chunk_of[kMaxChunkSlots];
 };
 #ifdef __HIPCC__
 struct AttnWork {

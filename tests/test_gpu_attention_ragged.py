@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
     (4, 1, 16, 128, "bf16", "bf16", [2049, 17, 2048]),
     (8, 8, 64, 128, "bf16", "int4", [5000, 130, 2600]),
     (2, 16, 32, 96, "f32", "f32", [1500, 33, 700, 0]),
-    (1, 2, 64, 128, "bf16", "bf16", [700 - i for i in range(200)])])                 # a large batch
+    (1, 2, 64, 128, "bf16", "bf16", [700 - i for i in range(200)]),                  # a large batch
+    (1, 2, 64, 128, "bf16", "bf16", [640, 64] + [640] * 198)])               # two chunks per sequence but one
 def test_mixed_lengths_match_single_sequences(Hkv, G, P, d, dtype, factors, lens):
     import torch
     import paper_2608_23843_amd as pk
