@@ -180,39 +180,55 @@ __device__ __forceinline__ int cq_rank(float key, int c, int grp) {
     return rho;
 }
 
-// One wavefront per workgroup, which looks through `per_wave` of the launch's
-// pages and decomposes the K and V halves of those that are marked, clearing
-// the mark: side by side at P = 32, in turn at P = 64. kAdapt (a cache with
+constexpr int kCqWaves = 4;   // most wavefronts per workgroup, each on its own
+
+// The wavefronts look through the pages of the launch, or at P = 64 through
+// their K and V halves (marked_candidate), decompose those that are marked and
+// clear the marks. K and V go side by side at P = 32. kAdapt (a cache with
 // adaptive ranks): a rank of 0 asks for the rank chosen from the spectrum;
 // the packed factor slot places V's sections after K's rank, so the V
-// decomposition of a page must know K's rank before it stores.
+// decomposition of a page must know K's rank before it stores: at P = 64 a
+// wavefront then takes a page's K and V in turn.
 template <typename TF, int P, bool kAdapt, bool kList>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(64 * kCqWaves) __attribute__((amdgpu_waves_per_eu(3)))
 void k_compress_qr(Geo g, pkv_page *table, const char *dense, char *factor, CompressItems items, CompressSrc src,
-                   int64_t n_items, int per_wave) {
+                   int64_t n_items) {
     static_assert(P == 32 || P == 64, "P = 32 or 64");
-    constexpr int kPasses = P == 64 ? 2 : 1;
+    constexpr bool kHalves = P == 64 && !kAdapt;       // a candidate is a page half, not a page
+    constexpr int kPasses = P == 64 && kAdapt ? 2 : 1;
     constexpr bool kQ4 = is_q4<TF>::value;
-    extern __shared__ float cq_smem[];
+    extern __shared__ float cq_lds[];
     const int d = g.d;
-    const int lane = threadIdx.x;
+    const int wave_in = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    float *cq_smem = cq_lds + wave_in * cq_wave_lds(d, kQ4);
     int *cq_tok = (int *)(cq_smem + 64 + 64 * 32 + 64);   // position -> token, per group
-    const int grp = P == 64 ? 0 : lane >> 5;
-    const int c = P == 64 ? lane : lane & 31;
-    const int64_t first = (int64_t)blockIdx.x * per_wave, last = min(first + per_wave, n_items);
-    for (int64_t base = first; base < last; base += 64) {
-    int64_t entry = -1;
+    const uint32_t waves = gridDim.x * (blockDim.x / 64), wave = blockIdx.x * (blockDim.x / 64) + wave_in;
+    const int64_t n_cand = kHalves ? 2 * n_items : n_items;
+    for (int64_t t0 = 0; t0 * waves < n_cand; t0 += 64) {
     bool marked = false;
-    if (base + lane < last) {
-        const CompressItem it = decode_item<kList>(g, items, src, base + lane);
-        entry = g.head_index(it.b, it.h) * g.max_pages + it.j;
-        marked = page_marked(g, table[entry]);
+    {
+        const int64_t cand = marked_candidate((uint32_t)t0 + (threadIdx.x & 63), wave, waves, n_cand);
+        if (cand < n_cand) {
+            const CompressItem it = decode_item<kList>(g, items, src, kHalves ? cand >> 1 : cand);
+            const pkv_page e = table[g.head_index(it.b, it.h) * g.max_pages + it.j];
+            marked = (page_marks(g, e) & (kHalves ? 1u << (cand & 1) : 3u)) != 0;
+        }
     }
     for (uint64_t left = __ballot(marked); left; left &= left - 1) {
-    const int64_t item = base + __builtin_ctzll(left);
+    // nothing per lane is kept from one page to the next: the decomposition has
+    // no register to spare
+    const int64_t item = marked_candidate((uint32_t)t0 + __builtin_ctzll(left), wave, waves, n_cand);
     int rk_first = 0;   // two passes: the K rank chosen by the first
     for (int kv = 0; kv < kPasses; ++kv) {
-    const int64_t q = 2 * item + (P == 64 ? kv : grp);
+    // the lane again, from a mask the compiler cannot see: it would otherwise
+    // compute everything that depends on it once for all pages and hold it (150
+    // registers, spilled to scratch memory)
+    int all = -1;
+    asm volatile("" : "+s"(all));
+    const int lane = __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));
+    const int grp = P == 64 ? 0 : lane >> 5;
+    const int c = P == 64 ? lane : lane & 31;
+    const int64_t q = kHalves ? item : 2 * item + (P == 64 ? kv : grp);
 
     const DecompRef ref = decode_decomp<uint16_t, kList>(g, table, dense, items, src, q, 2 * n_items, false);
     const bool active = ref.active;
@@ -824,25 +840,39 @@ void k_compress_qr(Geo g, pkv_page *table, const char *dense, char *factor, Comp
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
     }   // passes
-    }   // marked pages
     __builtin_amdgcn_wave_barrier();
-    if (marked) table[entry].rows &= (uint8_t)~1u;
-    }   // pages of this wavefront
+    if (__builtin_amdgcn_mbcnt_hi(-1, __builtin_amdgcn_mbcnt_lo(-1, 0)) == 0) {
+        const CompressItem it = decode_item<kList>(g, items, src, kHalves ? item >> 1 : item);
+        unmark_page(table + g.head_index(it.b, it.h) * g.max_pages + it.j, kHalves ? 1u << (item & 1) : 3u);
+    }
+    }   // marked candidates
+    }   // candidates of this wavefront
 }
 
-// The marked pages of a launch of n_items pages. A launch usually has none:
-// then a wavefront's work is one look at its pages' entries, up to 64 at a
-// time, and the launch costs its dispatch. 512 wavefronts: with 4,096 it took
-// 9 us on 4,080 pages and 19 us on 65,248, with 512 4 and 5 us; fewer would
-// leave a launch of marked pages alone with too few of the chip's SIMDs.
+// The marked pages of a launch of n_items pages. A launch usually has none: then
+// a wavefront's work is one look at its candidates' entries, up to 64 at a
+// time, and the launch costs its dispatch, 2 us for every 3,072 wavefronts that
+// the chip holds at a time. The decompositions take unequal times, so that a
+// grid of just those wavefronts waits for the unluckiest: four 128K prompts of
+// 8 KV heads with every page marked take 23.1 ms with 3,072, 22.0 with twice
+// and 21.3 with four times as many, 20.3 with one for each of the 130,496
+// halves; a 16K prompt at P = 32 538 and, with one for each of its 4,080 pages,
+// 502 us. So one grid's worth more for every 12,288 candidates, up to four,
+// which an unmarked prompt does not notice (one for each candidate: 125 -> 128
+// us on the 16K prompt, 4.56 -> 4.65 ms on the 128K ones). Four wavefronts per
+// workgroup; few candidates are spread over the CUs instead (1K tokens, every
+// page marked: 391 against 406 us).
 template <typename TF, int P, bool kAdapt, bool kList>
 hipError_t launch_compress_qr_marked(const LaunchCtx &L, const CompressItems &items, const CompressSrc &src,
                                      int64_t n_items) {
-    const size_t smem = (size_t)cq_wave_lds(L.geo.d, is_q4<TF>::value) * sizeof(float);
-    const int64_t per_wave = ceil_div(n_items, (int64_t)512);
+    const int64_t n_cand = P == 64 && !kAdapt ? 2 * n_items : n_items;
+    const int per_block = n_cand <= 1024 ? 1 : kCqWaves;
+    const int64_t grids = std::max<int64_t>(1, std::min<int64_t>(4, n_cand / 12288));
+    const int64_t blocks = std::min<int64_t>(ceil_div(n_cand, per_block), per_block == 1 ? 1024 : grids * 3 * 256);
+    const size_t smem = (size_t)per_block * cq_wave_lds(L.geo.d, is_q4<TF>::value) * sizeof(float);
     const LayerPtrs p = layer_ptrs(L);
-    hipLaunchKernelGGL((k_compress_qr<TF, P, kAdapt, kList>), dim3((unsigned)ceil_div(n_items, per_wave)), dim3(64), smem,
-                       L.stream, L.geo, p.table, p.dense, p.factor, items, src, n_items, (int)per_wave);
+    hipLaunchKernelGGL((k_compress_qr<TF, P, kAdapt, kList>), dim3((unsigned)blocks), dim3(64 * per_block), smem,
+                       L.stream, L.geo, p.table, p.dense, p.factor, items, src, n_items);
     return hipGetLastError();
 }
 

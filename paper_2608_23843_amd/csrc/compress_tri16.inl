@@ -379,7 +379,7 @@ void k_compress_tri16(Geo g, pkv_page *table, const char *dense, char *factor, C
         const int t = v >> 1, which = v & 1;
         if (!active[t]) continue;
         if ((bad_half >> (2 * t)) & 3u) {   // to k_compress, both halves of the page
-            if (lane == 0 && which == 0) table[entry[t]].rows |= 1;
+            if (lane == 0 && which == 0) mark_page(table + entry[t], 3u);
             continue;
         }
         const int rk = rank[2 * t], rv = rank[2 * t + 1], rk4 = r4(rk), rv4 = r4(rv);

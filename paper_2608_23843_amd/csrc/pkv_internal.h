@@ -7,6 +7,7 @@
 
 #include "puzzlekv.h"
 #include "attention_plan.h"
+#include "marked_split.h"
 
 namespace pkv {
 

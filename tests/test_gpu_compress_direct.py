@@ -126,3 +126,44 @@ def test_16_token_pages_off_16_byte_rows():
     # rank r of a page's noise spectrum: its gaps are 1% or more, so the fp32
     # Gram's n eps |G| moves the products by 1e-4 at most
     assert (out[0] - out[1]).norm() <= 1e-4 * out[0].norm()
+
+
+@pytest.mark.parametrize("P,r,n,factors,eps", [(16, 6, 4500, "bf16", 0.0), (32, 12, 3300, "bf16", 0.0), (64, 24, 1700, "bf16", 0.0),
+                                               (64, 0, 3200, "bf16", 0.05), (64, 24, 1700, "int4", 0.0)])
+@pytest.mark.parametrize("which", ["K", "V", "both", "run"])
+def test_many_marked_pages(P, r, n, factors, eps, which):
+    """More marked pages than the launch over them has wavefronts, only one half of
+    them marked, and a run of them: each is factorized and no mark stays."""
+    import torch
+    import paper_2608_23843_amd as pk
+    d, g = 128, torch.Generator(device="cuda").manual_seed(P + n)
+    flat = torch.randn(n, 4, d, generator=g, device="cuda").repeat_interleave(P // 4, 1)   # four rows, repeated: rank 4
+    if eps:   # equal eigenvalues: rank 32 of 64 leaves half of the energy
+        flat = torch.from_numpy(3.0 * _hadamard(d)[:P]).float().cuda().expand(n, P, d)
+    # the other pages' planted singular values are a factor of two apart
+    full = torch.randn(n, P, 5, generator=g, device="cuda") @ (torch.randn(n, 5, d, generator=g, device="cuda") *
+                                                              2.0 ** torch.arange(5, device="cuda")[:, None])
+    full = full + 0.05 * torch.randn(n, P, d, generator=g, device="cuda")
+    run = torch.zeros(n, 1, 1, dtype=torch.bool, device="cuda")
+    run[n // 3:n // 3 + 130] = True
+    K = torch.where(run, flat, full) if which == "run" else flat if which in ("K", "both") else full
+    V = flat if which in ("V", "both") else full
+    k, v = (x.bfloat16().view(1, 1, n * P, d).contiguous() for x in (K, V))
+    cache = pk.PuzzleKVCache(1, 1, 1, 1, d, P, n, r or 32, 0, 0, "bf16", factors, adaptive_rank_error=eps)
+    cache.compress_sweeps()
+    cache.prefill(0, k, v, [n * P], default_rank=(r, r))
+    assert cache.device_status() == 0
+    assert cache.compress_sweeps() > 0
+    assert torch.all(cache.page_table(0)[0, 0, :n, 7] == 0)
+    R = r or 32
+    tol = {"bf16": 8e-3, "int4": 0.12}[factors]   # bf16: two roundings of 2^-9 per entry; INT4: of 1/14 of a run's largest
+    for i in range(0, n, 500):
+        m = min(500, n - i)
+        blk = cache.export_pages(0, [0] * m, [0] * m, list(range(i, i + m)))
+        o = 0
+        for x in (k, v):
+            X = x.view(n, P, d)[i:i + m].float()
+            Y = blk[:, o:o + P * R].reshape(m, P, R).contiguous() @ blk[:, o + P * R:o + (P + d) * R].reshape(m, R, d).contiguous()
+            o += (P + d) * R
+            err = (X - Y).flatten(1).norm(dim=1) / X.flatten(1).norm(dim=1)
+            assert float(err.max()) <= tol + (0.7072 if eps else 2e-2), (i, int(err.argmax()), float(err.max()))
