@@ -1,9 +1,9 @@
 // Per-page truncated decomposition by one-sided Jacobi for bf16 pages of
 // P = 32 or 64 tokens (Section 3.3, Eq. (2)). It takes the pages that
-// k_compress_tri marks, whose spectrum has eigenvalues too close together for
-// the direct method (repeated rows, rank below r, ranks above 32 at P = 64):
-// it needs three times the time per page, but converges on any spectrum. The
-// result is the top-r eigenvectors L of the page's Gram matrix G = X X^T and
+// k_compress_tri marks: those whose spectrum has eigenvalues too close together
+// for the direct method (repeated rows, rank below r), and at P = 64 those of
+// ranks above 32. It needs three times the time per page, but converges on any
+// spectrum. The result is the top-r eigenvectors L of the page's Gram matrix G = X X^T and
 // R = L^T X, reached in four phases per wavefront (one page half for P = 64,
 // two for P = 32, one per 32-lane half):
 //
@@ -188,8 +188,10 @@ constexpr int kCqWaves = 4;   // most wavefronts per workgroup, each on its own
 // adaptive ranks): a rank of 0 asks for the rank chosen from the spectrum;
 // the packed factor slot places V's sections after K's rank, so the V
 // decomposition of a page must know K's rank before it stores: at P = 64 a
-// wavefront then takes a page's K and V in turn.
-template <typename TF, int P, bool kAdapt, bool kList>
+// wavefront then takes a page's K and V in turn. kWide: ranks above 32 (P = 64;
+// caches with max_rank above 32), for which the eigenvectors outlive the first
+// 32 ranks' products (64 registers: others' marked pages would take 4% longer).
+template <typename TF, int P, bool kAdapt, bool kList, bool kWide>
 __global__ __launch_bounds__(64 * kCqWaves) __attribute__((amdgpu_waves_per_eu(3)))
 void k_compress_qr(Geo g, pkv_page *table, const char *dense, char *factor, CompressItems items, CompressSrc src,
                    int64_t n_items) {
@@ -584,10 +586,10 @@ void k_compress_qr(Geo g, pkv_page *table, const char *dense, char *factor, Comp
     }
 
     // ---- 5. R = L^T X and the stores -----------------------------------------
-    // L goes to LDS (sL[t][rank], 32 ranks, zero past r). Each lane then owns
-    // two output dims for every rank: one 4-byte load per page row (a row is
-    // one coalesced 256-byte read across the lanes) and 64 fmas against the
-    // row's L entries, read as broadcasts.
+    // L goes to LDS, 32 ranks at a time (sL[t][rank - r0], zero past r). Each
+    // lane then owns two output dims for each of them: one 4-byte load per page
+    // row (a row is one coalesced 256-byte read across the lanes) and 64 fmas
+    // against the row's L entries, read as broadcasts.
     // the page's K and V ranks (each chosen by its own half when adaptive)
     int rk, rv;
     if constexpr (P == 64) {
@@ -611,14 +613,17 @@ void k_compress_qr(Geo g, pkv_page *table, const char *dense, char *factor, Comp
     }
     float *sL = cq_smem + 64 + grp * (P * 32);   // this group's P x 32 block
     float *sInvSig = cq_smem + 64 + 64 * 32 + grp * 32;
+#pragma unroll 1
+    for (int r0 = 0; r0 == 0 || (kWide && r0 < r); r0 += 32) {
     {
         const float sig = sqrtf(fmaxf(lam, 0.f));
         const float scale = kQ4 ? sqrtf(sig) : 1.f;   // INT4: L~ = U Sigma^(1/2)
-        if (rho < 32) {
+        const int rs = kWide ? rho - r0 : rho;
+        if (rs >= 0 && rs < 32) {
             const int *tok = cq_tok + grp * P;
 #pragma unroll
-            for (int e = 0; e < P; ++e) sL[tok[e] * 32 + rho] = (rho < r && active) ? gc[e] * scale : 0.f;
-            sInvSig[rho] = sig > 0.f ? 1.f / sig : 0.f;
+            for (int e = 0; e < P; ++e) sL[tok[e] * 32 + rs] = (rho < r && active) ? gc[e] * scale : 0.f;
+            sInvSig[rs] = sig > 0.f ? 1.f / sig : 0.f;
         }
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
@@ -708,7 +713,7 @@ void k_compress_qr(Geo g, pkv_page *table, const char *dense, char *factor, Comp
                     uint16_t *Bk = Ak + fl.bk;             // R_K, rk x d: dims k, k + 1 side by side
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
-                        const int a = 8 * (v >> 2) + 4 * h + (v & 3);
+                        const int a = r0 + 8 * (v >> 2) + 4 * h + (v & 3);
                         if (a < rk) *(uint32_t *)(Bk + (int64_t)a * d + k) = cq_pack_bf16(ae[v], ao[v]);
                     }
                 } else {
@@ -718,7 +723,7 @@ void k_compress_qr(Geo g, pkv_page *table, const char *dense, char *factor, Comp
                     uint16_t *Bt = Ak + (which == 0 ? fl.bk : fl.bvt);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        const int a0 = 8 * j + 4 * h;
+                        const int a0 = r0 + 8 * j + 4 * h;
                         if (a0 >= rw) continue;
                         *(uint2 *)(Bt + (int64_t)k * rw + a0) =
                             make_uint2(cq_pack_bf16(ae[4 * j], ae[4 * j + 1]), cq_pack_bf16(ae[4 * j + 2], ae[4 * j + 3]));
@@ -795,25 +800,25 @@ void k_compress_qr(Geo g, pkv_page *table, const char *dense, char *factor, Comp
                 TF *Bkt = Ak + fl.bk;                      // R_K^T, d x r4(rk), zero past rk
 #pragma unroll
                 for (int a = 0; a < 32; ++a)
-                    if (a < rk4) {
-                        st(Bkt, (int64_t)k * rk4 + a, acc[0][a]);
-                        st(Bkt, (int64_t)(k + 1) * rk4 + a, acc[1][a]);
+                    if (r0 + a < rk4) {
+                        st(Bkt, (int64_t)k * rk4 + r0 + a, acc[0][a]);
+                        st(Bkt, (int64_t)(k + 1) * rk4 + r0 + a, acc[1][a]);
                     }
             } else if (which == 0) {
                 TF *Bk = Ak + fl.bk;                       // R_K, rk x d
 #pragma unroll
                 for (int a = 0; a < 32; ++a)
-                    if (a < rk) {
-                        st(Bk, (int64_t)a * d + k, acc[0][a]);
-                        st(Bk, (int64_t)a * d + k + 1, acc[1][a]);
+                    if (r0 + a < rk) {
+                        st(Bk, (int64_t)(r0 + a) * d + k, acc[0][a]);
+                        st(Bk, (int64_t)(r0 + a) * d + k + 1, acc[1][a]);
                     }
             } else {
                 TF *Bvt = Ak + fl.bvt;                     // R_V^T, d x r4(rv), zero past rv
 #pragma unroll
                 for (int a = 0; a < 32; ++a)
-                    if (a < rv4) {
-                        st(Bvt, (int64_t)k * rv4 + a, acc[0][a]);
-                        st(Bvt, (int64_t)(k + 1) * rv4 + a, acc[1][a]);
+                    if (r0 + a < rv4) {
+                        st(Bvt, (int64_t)k * rv4 + r0 + a, acc[0][a]);
+                        st(Bvt, (int64_t)(k + 1) * rv4 + r0 + a, acc[1][a]);
                     }
             }
         }
@@ -831,14 +836,15 @@ void k_compress_qr(Geo g, pkv_page *table, const char *dense, char *factor, Comp
         const int t = c;
         if (which == 0) {
             const int rk4 = r4(rk);
-            for (int a = 0; a < rk4; ++a) st(Ak, (int64_t)t * rk4 + a, sL[t * 32 + a]);
+            for (int a = r0; a < min(rk4, r0 + 32); ++a) st(Ak, (int64_t)t * rk4 + a, sL[t * 32 + a - r0]);
         } else {
             TF *Avt = Ak + fl.avt;
-            for (int a = 0; a < rv; ++a) st(Avt, (int64_t)a * P + t, sL[t * 32 + a]);
+            for (int a = r0; a < min(rv, r0 + 32); ++a) st(Avt, (int64_t)a * P + t, sL[t * 32 + a - r0]);
         }
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
+    }   // 32 ranks at a time
     }   // passes
     __builtin_amdgcn_wave_barrier();
     if (__builtin_amdgcn_mbcnt_hi(-1, __builtin_amdgcn_mbcnt_lo(-1, 0)) == 0) {
@@ -871,8 +877,11 @@ hipError_t launch_compress_qr_marked(const LaunchCtx &L, const CompressItems &it
     const int64_t blocks = std::min<int64_t>(ceil_div(n_cand, per_block), per_block == 1 ? 1024 : grids * 3 * 256);
     const size_t smem = (size_t)per_block * cq_wave_lds(L.geo.d, is_q4<TF>::value) * sizeof(float);
     const LayerPtrs p = layer_ptrs(L);
-    hipLaunchKernelGGL((k_compress_qr<TF, P, kAdapt, kList>), dim3((unsigned)blocks), dim3(64 * per_block), smem,
-                       L.stream, L.geo, p.table, p.dense, p.factor, items, src, n_items);
+    constexpr bool kMayBeWide = P == 64 && !is_q4<TF>::value;   // INT4 caches have no ranks above 32
+    const auto kernel = kMayBeWide && L.geo.max_rank > 32 ? k_compress_qr<TF, P, kAdapt, kList, kMayBeWide>
+                                                          : k_compress_qr<TF, P, kAdapt, kList, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * per_block), smem, L.stream, L.geo, p.table, p.dense,
+                       p.factor, items, src, n_items);
     return hipGetLastError();
 }
 

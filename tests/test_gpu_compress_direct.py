@@ -38,7 +38,8 @@ def _pages(P, d, rng):
             ("white noise", rng.standard_normal((P, d)))]
 
 
-@pytest.mark.parametrize("P,d,r", [(16, 32, 1), (16, 64, 4), (16, 128, 9), (16, 256, 16), (32, 64, 1), (32, 128, 14), (32, 32, 16), (64, 64, 8), (64, 128, 24), (64, 256, 32)])
+@pytest.mark.parametrize("P,d,r", [(16, 32, 1), (16, 64, 4), (16, 128, 9), (16, 256, 16), (32, 64, 1), (32, 128, 14), (32, 32, 16), (64, 64, 8), (64, 128, 24), (64, 256, 32),
+                                   (64, 128, 33), (64, 128, 48), (64, 64, 64)])
 @pytest.mark.parametrize("factors", ["bf16", "f32"])
 @pytest.mark.parametrize("how", ["prefill", "compress"])
 def test_direct_decomposition_and_marked_pages(P, d, r, factors, how):
@@ -167,3 +168,48 @@ def test_many_marked_pages(P, r, n, factors, eps, which):
             o += (P + d) * R
             err = (X - Y).flatten(1).norm(dim=1) / X.flatten(1).norm(dim=1)
             assert float(err.max()) <= tol + (0.7072 if eps else 2e-2), (i, int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("factors", ["bf16", "f32"])
+@pytest.mark.parametrize("eps", [0.0, 0.01])
+def test_ranks_above_32(factors, eps):
+    """Pages of 64 tokens whose halves ask for, or with adaptive ranks need, ranks on both sides of 32."""
+    import torch
+    import paper_2608_23843_amd as pk
+    P, d, n = 64, 128, 12
+    planted = [(40, 8), (8, 40), (48, 48), (12, 12), (64, 33), (33, 64)] * 2
+    rng = np.random.default_rng(17)
+    X = np.zeros((2, n, P, d))
+    for j, rr in enumerate(planted):
+        for w, r in enumerate(rr):   # singular values within a factor of two, then noise below the error asked for
+            q1, q2 = (np.linalg.qr(rng.standard_normal((s, r)))[0] for s in (P, d))
+            X[w, j] = 50.0 * (q1 * np.linspace(1.0, 0.5, r)) @ q2.T + 1e-3 * rng.standard_normal((P, d))
+    X = storage_round(X, "bf16")
+    k, v = (torch.from_numpy(x).to("cuda", torch.bfloat16).reshape(1, 1, n * P, d).contiguous() for x in X)
+    cache = pk.PuzzleKVCache(1, 1, 1, 1, d, P, n, 64, 0, 0, "bf16", factors, adaptive_rank_error=eps)
+    want = np.asarray(planted, dtype=np.uint8)
+    if eps:
+        cache.prefill(0, k, v, [n * P], default_rank=(0, 0))
+    else:
+        rk, rv = (torch.from_numpy(np.ascontiguousarray(want[:, w]).reshape(1, 1, n)).cuda() for w in (0, 1))
+        cache.prefill(0, k, v, [n * P], rank_k=rk, rank_v=rv)
+    assert cache.device_status() == 0
+    table = cache.page_table(0).cpu().numpy()[0, 0]
+    assert np.all(table[:, 7] == 0)
+    if not eps:
+        assert np.array_equal(table[:, 5:7], want)
+    blk = cache.export_pages(0, [0] * n, [0] * n, list(range(n))).cpu().numpy().astype(np.float64)
+    rec_tol, orth_tol, _ = TOL[factors]
+    for j in range(n):
+        o = 0
+        for w in (0, 1):
+            r, Y = int(table[j, 5 + w]), X[w, j].astype(np.float64)
+            L, R = blk[j][o:o + P * 64].reshape(P, 64), blk[j][o + P * 64:o + (P + d) * 64].reshape(64, d)
+            o += (P + d) * 64
+            assert np.all(L[:, r:] == 0) and np.all(R[r:] == 0)
+            assert np.abs(L[:, :r].T @ L[:, :r] - np.eye(r)).max() <= orth_tol
+            s = np.linalg.svd(Y, compute_uv=False)
+            tail, norm = np.sqrt(np.sum(s[r:] ** 2)), np.linalg.norm(Y)
+            assert np.linalg.norm(Y - L @ R) <= (1 + 1e-3) * tail + rec_tol * norm
+            if eps:   # the smallest rank within the error
+                assert tail <= eps * 1.001 * norm and np.sqrt(np.sum(s[r - 1:] ** 2)) >= eps * 0.999 * norm
