@@ -10,7 +10,7 @@ namespace pkv {
 // final merge short.
 static int attention_sched(const Geo &g, int pages_per_chunk);
 
-// The plan when every sequence has max_T tokens; it sizes the workspace.
+// The plan when every sequence has max_T tokens; it sizes the call's partial states.
 AttnPlan attention_plan(const Geo &g, int64_t max_T) {
     AttnPlan p{};
     const int64_t n_pages = std::max<int64_t>(1, ceil_div(max_T, g.P));
@@ -53,7 +53,17 @@ static int attention_sched(const Geo &g, int pages_per_chunk) {
     return (wave_claims ? kSchedWaveClaims : 0) | (short_stream && wave_claims ? 0 : kSchedReverse);
 }
 
+// For the geometries of the generic kernel a workspace for max_T tokens holds
+// the states of every shorter length too (until it aimed at 256 workgroups
+// instead of 1,024, shorter lengths needed more only beyond 1,024 pages over
+// all heads).
 int64_t attention_workspace_bytes(const Geo &g, int64_t max_T) {
+    if (mfma_supported(g)) return attention_call_bytes(g, max_T);
+    const int n = most_chunks(g.B, g.Hkv, std::max<int64_t>(1, ceil_div(max_T, g.P)));
+    return partials_bytes((int64_t)g.B * g.Hkv, n, g.g, g.d);
+}
+
+int64_t attention_call_bytes(const Geo &g, int64_t max_T) {
     const AttnPlan p = attention_plan(g, max_T);
     return partials_bytes((int64_t)g.B * g.Hkv, p.n_chunks, g.g, g.d);
 }

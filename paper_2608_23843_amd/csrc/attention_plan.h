@@ -49,6 +49,13 @@ inline ChunkPlan chunk_plan_equal(int B, int Hkv, int64_t n_pages) {
     return {(int)ppc, (int)ceil_div(n_pages, ppc), true};
 }
 
+// The most chunks of a head among plans of equal lengths up to n_pages pages.
+// The number is not monotone: 8 heads have 32 chunks of one page at 32 pages and
+// 17 of two at 33.
+inline int most_chunks(int B, int Hkv, int64_t n_pages) {
+    return (int)std::min(n_pages, ceil_div(kAttnGroups, (int64_t)B * Hkv));
+}
+
 // The plan for these lengths; `full` is that of equal lengths, all the longest.
 // The pages per chunk come from the pages there are, not from the longest
 // sequence times the batch: in a batch of mixed lengths the long heads would

@@ -421,7 +421,7 @@ pkv_status pkv_mixed_decode_attention(const pkv_cache *c, int32_t layer, const v
         max_T = std::max<int64_t>(max_T, seq_len[b]);
     }
     LaunchCtx L = ctx(c, layer, s);
-    size_t need = (size_t)attention_workspace_bytes(L.geo, max_T);
+    size_t need = (size_t)attention_call_bytes(L.geo, max_T);
     if ((st = check_ws(ws, ws_bytes, need)) != PKV_OK) return st;
     AttnPlan plan = attention_plan(L.geo, max_T);
     return check_launch(launch_attention(L, plan, q, seq, out, lse, ws), "pkv_mixed_decode_attention");

@@ -262,7 +262,10 @@ struct AttnPlan {
 // than per workgroup round; pages handed out last to first.
 constexpr int kSchedWaveClaims = 1, kSchedReverse = 2;
 AttnPlan attention_plan(const Geo &g, int64_t max_T);
+// Bytes of a workspace for calls of up to max_T tokens, and those that a call
+// whose longest sequence has max_T tokens uses.
 int64_t attention_workspace_bytes(const Geo &g, int64_t max_T);
+int64_t attention_call_bytes(const Geo &g, int64_t max_T);
 // Partial-state bytes the calls without a workspace can use, and the bytes
 // such a call needs for its geometry and longest sequence.
 int64_t scratch_state_bytes();

@@ -251,3 +251,15 @@ def test_bandwidth_probe_argument_errors(pk):
     assert lib.pkv_bandwidth_probe(vp(0x1008), vp(0x2000), 1024, 0, 1, 64, 256, ctypes.byref(g), None) == 1
     assert lib.pkv_bandwidth_probe(vp(0x1000), vp(0x2000), 1024, 4, 1, 64, 256, ctypes.byref(g), None) == 1
     assert lib.pkv_bandwidth_probe(vp(0x1000), vp(0x2000), 1024, 0, 1, 64, 100, ctypes.byref(g), None) == 1
+
+
+@pytest.mark.parametrize("kw", [dict(batch=1, n_kv_heads=8, n_q_heads=32, dense_dtype=0, factor_dtype=0),
+                                dict(batch=3, n_kv_heads=2, n_q_heads=4, head_dim=192),
+                                dict(batch=200, n_kv_heads=1, n_q_heads=1, dense_dtype=0, factor_dtype=0)])
+def test_generic_workspace_serves_shorter_lengths(pk, kw):
+    """A workspace for n tokens is at least that for any shorter length (fp32
+    storage and other geometries of the generic attention kernel)."""
+    lib = pk.load_library()
+    c = _cache(pk, max_pages=4096, **kw)
+    sizes = [lib.pkv_workspace_bytes(c, 0, 64 * n) for n in range(1, 1200)]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
