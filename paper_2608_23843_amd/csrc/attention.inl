@@ -365,14 +365,18 @@ __device__ __forceinline__ void gen_lds_order() {
     __builtin_amdgcn_wave_barrier();
 }
 // 16 stored rows times the query group over d dims: lane (n, q) reads row n at
-// p. Past d (d <= 16 DT) the last dims are read again, against zero queries.
+// p. Past d (d <= 16 DT) the last dims are read again and not used.
 template <int DT, typename T>
 __device__ __forceinline__ f32x4 gen_rows(const T *p, const float *sq, int d) {
     f32x4 a[DT], c = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < DT; ++s) a[s] = gen_ld4(p + min(16 * s, d - 16));
 #pragma unroll
-    for (int s = 0; s < DT; ++s) c = gen_mfma(a[s], *(const f32x4 *)(sq + 16 * s), c);
+    for (int s = 0; s < DT; s += 2)   // d is a multiple of 32, above 8 DT (32 for DT = 4)
+        if (s < (DT == 4 ? 2 : DT / 2 + 2) || 16 * s < d) {
+            c = gen_mfma(a[s], *(const f32x4 *)(sq + 16 * s), c);
+            c = gen_mfma(a[s + 1], *(const f32x4 *)(sq + 16 * s + 16), c);
+        }
     return c;
 }
 // o[t] += 16 stored columns times b: lane (n, q) reads entries of dim 16 t + n

@@ -81,3 +81,28 @@ def test_generic_attention(dense, factors, d, P, G, rk, rv, pages):
             got = out[b, h * G:(h + 1) * G]
             assert np.linalg.norm(got - ro) <= REL * np.linalg.norm(ro), (b, h)
             assert np.abs(lse[b, h * G:(h + 1) * G] - rl).max() <= REL * max(1.0, np.abs(rl).max())
+
+
+@pytest.mark.parametrize("dense,d,P", [("f32", 96, 32), ("bf16", 160, 64), ("f32", 32, 16)])
+def test_minus_infinity_key_entries(dense, d, P):
+    """Keys whose last dims hold -inf where the query is positive score -inf and get no
+    weight, also where the head is not a whole number of the kernel's dim tiles."""
+    import torch
+    import paper_2608_23843_amd as pk
+    Hkv, G, T = 2, 3, 5 * P - 7
+    g = torch.Generator(device="cuda").manual_seed(d)
+    cache = pk.PuzzleKVCache(1, 1, Hkv, Hkv * G, d, P, 5, 4, P, 5 * P, dense, dense)   # every page in the window
+    k, v = (torch.randn(1, Hkv, T, d, generator=g, device="cuda").to(cache.qdtype) for _ in range(2))
+    q = torch.randn(1, Hkv * G, d, generator=g, device="cuda").to(cache.qdtype)
+    q[..., -3] = q[..., -3].abs() + 0.1
+    out_at = torch.arange(T, device="cuda") % 3 == 1
+    k[:, :, out_at, -3] = -float("inf")
+    cache.prefill(0, k, v, [T], default_rank=(1, 1))
+    out, lse = cache.attention(0, q, [T])
+    assert cache.device_status() == 0
+    for h in range(Hkv):
+        kk, vv = k[0, h, ~out_at].double(), v[0, h, ~out_at].double()
+        s = q[0, h * G:(h + 1) * G].double() @ kk.T.contiguous() / d ** 0.5
+        ref = torch.softmax(s, 1) @ vv
+        assert (out[0, h * G:(h + 1) * G].double() - ref).norm() <= REL * ref.norm()
+        assert (lse[0, h * G:(h + 1) * G].double() - torch.logsumexp(s, 1)).abs().max() <= REL * 10
