@@ -72,6 +72,11 @@ __device__ inline void cq_split2(float a, float b, uint32_t &hi, uint32_t &lo) {
     hi = cq_pack_bf16(a, b);
     lo = cq_pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
 }
+// Two fp32 values as three bf16 pairs, which hold all 24 bits.
+__device__ inline void cq_split3(float a, float b, uint32_t &hi, uint32_t &mid, uint32_t &lo) {
+    hi = cq_pack_bf16(a, b);
+    cq_split2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u), mid, lo);
+}
 // Page dims k and k + 1 (k even) over tokens t0..t0+7 as two MFMA operands:
 // one 4-byte read per token row, split into its even and odd dim.
 __device__ inline void cq_load_dim_pair(const uint16_t *X, bool transposed, int P, int d, int k, int t0,

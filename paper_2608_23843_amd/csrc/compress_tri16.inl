@@ -328,7 +328,8 @@ void k_compress_tri16(Geo g, pkv_page *table, const char *dense, char *factor, C
             Z[4 * v + 3] = fmaf(-st[v], ub[v].w, Z[4 * v + 3]);
         }
     }
-    constexpr float kTol = std::is_same<TF, uint16_t>::value ? 1e-4f : 3e-7f;
+    // bf16 factors: where k_compress stops for them, 10 P 2^-23
+    constexpr float kTol = std::is_same<TF, uint16_t>::value ? 1.9e-5f : 3e-7f;
     for (int it = 0; it < 12; ++it) {
         c16_f32x4 S[4];
         float e = 0.f;
@@ -410,10 +411,11 @@ void k_compress_tri16(Geo g, pkv_page *table, const char *dense, char *factor, C
                 }
             }
         } else {
-            // L as bf16 hi + lo against the exact page; dims k and k + 1 per lane
-            uint32_t hw[2], lw[2];
-            cq_split2(Z[4 * v], Z[4 * v + 1], hw[0], lw[0]);
-            cq_split2(Z[4 * v + 2], Z[4 * v + 3], hw[1], lw[1]);
+            // L in three bf16 parts (all its bits) against the exact page; dims k and k + 1 per lane
+            uint32_t hw[2], mw[2], lw[2];
+            cq_split3(Z[4 * v], Z[4 * v + 1], hw[0], mw[0], lw[0]);
+            cq_split3(Z[4 * v + 2], Z[4 * v + 3], hw[1], mw[1], lw[1]);
+            const c16_s16x4 lmid = __builtin_bit_cast(c16_s16x4, make_uint2(mw[0], mw[1]));
             const c16_s16x4 lhi = __builtin_bit_cast(c16_s16x4, make_uint2(hw[0], hw[1]));
             const c16_s16x4 llo = __builtin_bit_cast(c16_s16x4, make_uint2(lw[0], lw[1]));
             for (int k = 2 * c; k < d; k += 32) {
@@ -432,6 +434,8 @@ void k_compress_tri16(Geo g, pkv_page *table, const char *dense, char *factor, C
                 c16_f32x4 ae = {}, ao = {};
                 ae = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(lhi, be, ae, 0, 0, 0);
                 ao = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(lhi, bo, ao, 0, 0, 0);
+                ae = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(lmid, be, ae, 0, 0, 0);
+                ao = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(lmid, bo, ao, 0, 0, 0);
                 ae = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(llo, be, ae, 0, 0, 0);
                 ao = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(llo, bo, ao, 0, 0, 0);
                 if (which == 0) {   // R_K, rk x d

@@ -213,3 +213,33 @@ def test_ranks_above_32(factors, eps):
             assert np.linalg.norm(Y - L @ R) <= (1 + 1e-3) * tail + rec_tol * norm
             if eps:   # the smallest rank within the error
                 assert tail <= eps * 1.001 * norm and np.sqrt(np.sum(s[r - 1:] ** 2)) >= eps * 0.999 * norm
+
+
+@pytest.mark.parametrize("P,points", [(16, [((2, 2, 7), 28)]),
+                                      (32, [((13, 1, 12), 36), ((4, 2, 12), 36), ((7, 10, 9), 36), ((6, 7, 12), 43),
+                                            ((0, 3, 15), 40), ((9, 2, 15), 40), ((5, 1, 12), 50), ((14, 0, 12), 50)])])
+def test_projection_holds_all_bits_of_l(P, points):
+    """R = L^T X for bf16 factors is the rounding of products with L in 24 bits.
+    Rank-1 pages a b^T with n1, n3, n5 tokens of 1, 3, 5: R = |a| b, at b where
+    |a| b lies 2e-6 or more off a rounding boundary of bf16 and products with L
+    in 16 bits (two bf16 parts) fall on its other side. fp32 gives |a| to a few 1e-7."""
+    import torch
+    import paper_2608_23843_amd as pk
+    d, n = 64, len(points)
+    X, want = np.zeros((n, P, d), dtype=np.float32), np.zeros((n, d))
+    for i, (cnt, m) in enumerate(points):
+        a = np.repeat([1.0, 3.0, 5.0], cnt)
+        a = np.concatenate([a, np.zeros(P - len(a))])
+        b = m * np.where(np.arange(d) % 3 == 0, -1.0, 1.0)
+        X[i] = a[:, None] * b
+        assert np.array_equal(storage_round(X[i], "bf16"), X[i])
+        want[i] = storage_round(np.linalg.norm(a) * b, "bf16")
+    x = torch.from_numpy(X).to("cuda", torch.bfloat16).reshape(1, 1, n * P, d).contiguous()
+    cache = pk.PuzzleKVCache(1, 1, 1, 1, d, P, n, 1, 0, 0, "bf16", "bf16")
+    cache.compress_sweeps()
+    cache.prefill(0, x, x, [n * P], default_rank=(1, 1))
+    assert cache.device_status() == 0 and cache.compress_sweeps() == 0
+    blk = cache.export_pages(0, [0] * n, [0] * n, list(range(n)))[:, :2 * (P + d)].cpu().numpy().reshape(n, 2, P + d)
+    for w in (0, 1):
+        R = blk[:, w, P:] * np.where(blk[:, w, P:P + 1] * want[:, :1] < 0, -1, 1)   # the sign of the vector is free
+        assert np.array_equal(R, want), (w, np.argwhere(R != want)[:4])
