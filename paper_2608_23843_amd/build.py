@@ -13,7 +13,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libpuzzlekv.so")
 
 SOURCES = ["pkv_kernels.hip", "pkv_host.cpp"]
-DEPS = ["pkv_internal.h", "attention_plan.h", "marked_split.h", "cache_ops.inl", "int4.inl", "compress.inl", "compress_qr.inl", "compress_tri.inl", "compress_tri16.inl", "attention.inl", "attention_mfma.inl", "attention_q4.inl",
+DEPS = ["pkv_internal.h", "attention_plan.h", "marked_split.h", "newton_schulz.h", "cache_ops.inl", "int4.inl", "compress.inl", "compress_qr.inl", "compress_tri.inl", "compress_tri16.inl", "attention.inl", "attention_mfma.inl", "attention_q4.inl",
         "attention_launch.inl", "global_svd.inl", "bandwidth.inl"]
 
 

@@ -330,24 +330,32 @@ void k_compress_tri16(Geo g, pkv_page *table, const char *dense, char *factor, C
     }
     // bf16 factors: where k_compress stops for them, 10 P 2^-23
     constexpr float kTol = std::is_same<TF, uint16_t>::value ? 1.9e-5f : 3e-7f;
-    for (int it = 0; it < 12; ++it) {
+    for (int it = 0;; ++it) {
         c16_f32x4 S[4];
-        float e = 0.f;
+        bool more = false, last = true;   // a half that needs this step, and one after it
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             S[v] = c16_f32x4{};
 #pragma unroll
             for (int i = 0; i < 4; ++i) S[v] = c16_mfma4(Z[4 * v + i], Z[4 * v + i], S[v]);
             bool bad = false;
+            float e = 0.f, f2 = 0.f;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float ei = fabsf(S[v][i] - (4 * b + i == c && c < rank[v] ? 1.f : 0.f));
-                bad = bad || !(ei <= kCtOrthMax);
-                e = fmaxf(e, bad ? 0.f : ei);
+                bad = bad || !(ei <= kOrthMax);
+                e = fmaxf(e, ei);
+                f2 = fmaf(ei, ei, f2);
             }
-            bad_half |= __any(bad) ? 1u << v : 0u;
+            const Orth next = orth_next(!__any(bad), !__any(e > kTol), 0.75f * ct_sum<64>(f2) <= kTol, it);
+            if (next == Orth::fail) {   // left to k_compress: the others go on without it
+                bad_half |= 1u << v;
+            } else if (((bad_half >> v) & 1u) == 0) {
+                more = more || next != Orth::done;
+                last = last && next != Orth::step;
+            }
         }
-        if (!__any(e > kTol)) break;
+        if (!more) break;
         ct_lds_fence();
 #pragma unroll
         for (int v = 0; v < 4; ++v)
@@ -365,7 +373,7 @@ void k_compress_tri16(Geo g, pkv_page *table, const char *dense, char *factor, C
 #pragma unroll
             for (int i = 0; i < 4; ++i) Z[4 * v + i] = y[i];
         }
-        if (!__any(e * e > kTol)) break;   // more than this step left
+        if (last) break;
     }
 
     // ---- 6. R = L^T X, stores --------------------------------------------------------------

@@ -8,6 +8,7 @@
 #include "puzzlekv.h"
 #include "attention_plan.h"
 #include "marked_split.h"
+#include "newton_schulz.h"
 
 namespace pkv {
 
