@@ -5,8 +5,8 @@
 // half b in register 4 b + i. Vectors are one element per lane (lane 16 b + c:
 // element c of half b), which is also the operand form of that product, so the
 // rank-2 update of all four halves is two products with no data movement, and
-// the products G u of the four halves are 16 fmas and three swaps. fp32 and
-// bf16 factors; pages whose eigenvalues cannot be told apart are marked for
+// the products G u of the four halves are 16 fmas and three swaps (fp32 factors:
+// in fp64 on the vector ALU). Pages whose eigenvalues cannot be told apart are marked for
 // k_compress.
 // What bounds it: vector-ALU issue and, with one page's work so short, the
 // page reads of the first and last phase. Measured against Jacobi in fp32
@@ -22,8 +22,12 @@ typedef float c16_f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kC16ZStride = 20;   // LDS row of a token's 16 vector entries
 // LDS floats: 14 reflectors of 16 elements per half, (d, e) and (d, e^2) pairs
-// of T; then, in the same place, the vectors by token row.
-constexpr int kC16Lds = 4 * 14 * 16 + 2 * 128 > 4 * 16 * kC16ZStride ? 4 * 14 * 16 + 2 * 128 : 4 * 16 * kC16ZStride;
+// of T (f64: and a step's u and w in fp64); then, in the same place, the vectors
+// by token row.
+constexpr int c16_lds(bool f64) {
+    const int tri = 4 * 14 * 16 + 2 * 128 + (f64 ? 256 : 0), z = 4 * 16 * kC16ZStride;
+    return tri > z ? tri : z;
+}
 
 __device__ __forceinline__ cq_f32x16 c16_outer(float a, float b, cq_f32x16 c) {
     return __builtin_amdgcn_mfma_f32_16x16x1f32(a, b, c, 0, 0, 0);
@@ -43,12 +47,81 @@ __device__ __forceinline__ float c16_row_sums(float t0, float t1, float t2, floa
     return s.a + s.b;
 }
 
+__device__ __forceinline__ double c16_row_sums(double t0, double t1, double t2, double t3) {
+    const ct_pair64 x = ct_swap32(t0, t2), y = ct_swap32(t1, t3);
+    const double a = x.a + x.b, b = y.a + y.b;
+    const auto l = __builtin_amdgcn_permlane16_swap(ct_lo(a), ct_lo(b), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(ct_hi(a), ct_hi(b), false, false);
+    return ct_join(l[0], h[0]) + ct_join(l[1], h[1]);
+}
+
+// The tridiagonalization in fp64, for fp32 factors (ct_tridiagonalize64 says
+// why). G: the fp32 Gram matrices, iu[v] the scale of half v. dv, ev: element c
+// of T's diagonal and off-diagonal.
+__device__ __forceinline__ void c16_tridiagonalize64(const cq_f32x16 &G, const float (&iu)[4], float *sV, double *sU,
+                                                     float &dv, float &ev) {
+    constexpr int P = 16;
+    const int lane = threadIdx.x, c = lane & 15, b = lane >> 4;
+    ct_f64x16 D;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) D[i] = (double)G[i] * (double)iu[i >> 2];
+    auto row = [&](int k) -> double {
+        const int i = k & 3;
+        const ct_pair64 x = ct_swap32(D[i], D[8 + i]), y = ct_swap32(D[4 + i], D[12 + i]);
+        const double p = (k & 8) ? x.b : x.a, q = (k & 8) ? y.b : y.a;
+        const auto l = __builtin_amdgcn_permlane16_swap(ct_lo(p), ct_lo(q), false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(ct_hi(p), ct_hi(q), false, false);
+        return (k & 4) ? ct_join(l[1], h[1]) : ct_join(l[0], h[0]);
+    };
+    double tri_d = 0.0, tri_e = 0.0;
+#pragma unroll 1
+    for (int k = 0; k < P - 2; ++k) {
+        const double rw = row(k);
+        const double x1 = __shfl(rw, (lane & 48) + k + 1, 64);
+        const double x = c > k ? rw : 0.0;
+        const double s2 = ct_sum<16>(x * x);
+        const double alpha = s2 > 1e-60 ? -__builtin_copysign(s2 * ct_rsq(s2), x1) : 0.0;
+        tri_d = c == k ? rw : tri_d;
+        tri_e = c == k ? alpha : tri_e;
+        const double hh = fma(fabs(x1), fabs(alpha), s2);
+        const double y = hh > 1e-36 ? ct_rsq(hh) : 0.0;
+        const double u = (c == k + 1 ? x1 - alpha : x) * y;
+        sV[(b * 14 + k) * 16 + c] = (float)u;
+        sU[lane] = u;
+        ct_lds_fence();
+        double t[4];
+        ct_f64x4 ub[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            ub[v] = ct_ld4(sU + 16 * v + 4 * b);   // rows 4 q .. of half v
+            t[v] = fma(D[4 * v], ub[v][0], fma(D[4 * v + 1], ub[v][1], fma(D[4 * v + 2], ub[v][2], D[4 * v + 3] * ub[v][3])));
+        }
+        const double p = c > k ? c16_row_sums(t[0], t[1], t[2], t[3]) : 0.0;
+        const double w = fma(-0.5 * ct_sum<16>(p * u), u, p);
+        sU[64 + lane] = w;
+        ct_lds_fence();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const ct_f64x4 wb = ct_ld4(sU + 64 + 16 * v + 4 * b);
+            const double uc = sU[16 * v + c], wc = sU[64 + 16 * v + c];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) D[4 * v + i] = fma(-wb[i], uc, fma(-ub[v][i], wc, D[4 * v + i]));
+        }
+        ct_lds_fence();
+    }
+    const double r0 = row(P - 2), r1 = row(P - 1);
+    const double e0 = __shfl(r0, (lane & 48) + P - 1, 64);
+    dv = (float)(c == P - 2 ? r0 : c == P - 1 ? r1 : tri_d);
+    ev = (float)(c == P - 2 ? e0 : c == P - 1 ? 0.0 : tri_e);
+}
+
 template <typename TF, bool kList>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
 void k_compress_tri16(Geo g, pkv_page *table, const char *dense, char *factor, CompressItems items, CompressSrc src,
                       int64_t n_items) {
     constexpr int P = 16;
-    __shared__ __align__(16) float smem[kC16Lds];
+    constexpr bool kF64 = ct_f64<TF>();
+    __shared__ __align__(32) float smem[c16_lds(kF64)];
     const int d = g.d;
     const int lane = threadIdx.x, c = lane & 15, b = lane >> 4;   // element c of half b; also column n and rows 4 q
     float *sV = smem;                        // reflector k of half b at (b * 14 + k) * 16
@@ -111,17 +184,17 @@ void k_compress_tri16(Geo g, pkv_page *table, const char *dense, char *factor, C
         fro2 = ct_sum<16>(c16_row_sums(f[0], f[1], f[2], f[3]));
     }
     const float gnorm = sqrtf(fro2);
-    {
-        const float ginv = gnorm > 0.f ? 1.f / gnorm : 0.f;
+    float iu[4];   // 1 / |G|_F of every half
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float iu = cq_f(__builtin_amdgcn_readlane(cq_i(ginv), 16 * u));
-#pragma unroll
-            for (int i = 0; i < 4; ++i) G[4 * u + i] *= iu;
-        }
-    }
+    for (int u = 0; u < 4; ++u) iu[u] = cq_f(__builtin_amdgcn_readlane(cq_i(gnorm > 0.f ? 1.f / gnorm : 0.f), 16 * u));
 
     // ---- 2. tridiagonalization -----------------------------------------------------
+    float dv = 0.f, ev = 0.f;   // T's diagonal and, below it, its off-diagonal, element c
+    if constexpr (kF64) {
+        c16_tridiagonalize64(G, iu, sV, (double *)(sQ + 256), dv, ev);
+    } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) G[i] *= iu[i >> 2];
     // row k of every half, one element per lane: from lane row k / 4
     auto row = [&](int k) -> float {
         const int i = k & 3;
@@ -129,7 +202,6 @@ void k_compress_tri16(Geo g, pkv_page *table, const char *dense, char *factor, C
         const ct_pair s = (k & 8) ? c16_swap16(x.b, y.b) : c16_swap16(x.a, y.a);
         return (k & 4) ? s.b : s.a;
     };
-    float dv = 0.f, ev = 0.f;   // T's diagonal and, below it, its off-diagonal, element c
     for (int k = 0; k < P - 2; ++k) {
         const float rw = row(k);
         const float x1 = __shfl(rw, (lane & 48) + k + 1, 64);
@@ -156,11 +228,12 @@ void k_compress_tri16(Geo g, pkv_page *table, const char *dense, char *factor, C
         G = c16_outer(u, -w, G);
         G = c16_outer(w, -u, G);
     }
+    const float r0 = row(P - 2), r1 = row(P - 1);
+    const float e0 = __shfl(r0, (lane & 48) + P - 1, 64);
+    dv = c == P - 2 ? r0 : c == P - 1 ? r1 : dv;
+    ev = c == P - 2 ? e0 : c == P - 1 ? 0.f : ev;
+    }   // fp32
     {
-        const float r0 = row(P - 2), r1 = row(P - 1);
-        const float e0 = __shfl(r0, (lane & 48) + P - 1, 64);
-        dv = c == P - 2 ? r0 : c == P - 1 ? r1 : dv;
-        ev = c == P - 2 ? e0 : c == P - 1 ? 0.f : ev;
         const float before = __shfl(ev, (lane & 48) + ((c + 15) & 15), 64);   // e_{c-1}; e_{15} = 0
         ((float2 *)sQ)[lane] = make_float2(dv, ev);
         sT[lane] = make_float2(dv, fmaxf(before * before, 1e-36f));
@@ -199,7 +272,7 @@ void k_compress_tri16(Geo g, pkv_page *table, const char *dense, char *factor, C
         int lo = above > 0 ? lo0 + kStep * (above - 1) : 0;
         int hi = above < 16 ? lo0 + kStep * above : hi0;
         const float frac = (float)((c & (lpe - 1)) + 1) / (float)(lpe + 1);
-        for (int it = 0; it < 32 && __any(j < r_own && hi - lo > kCtSectionUlps && lo > 0); ++it) {
+        for (int it = 0; it < 32 && __any(j < r_own && hi - lo > ct_section_ulps(kF64) && lo > 0); ++it) {
             const int m = lo + (int)((float)(hi - lo) * frac);
             const bool up = count(__int_as_float(m)) > j;
             int nl = up ? m : lo, nh = up ? hi : m;
@@ -376,6 +449,21 @@ void k_compress_tri16(Geo g, pkv_page *table, const char *dense, char *factor, C
         if (last) break;
     }
 
+    if constexpr (kF64) {   // unit length
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            double nn = 0.0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) nn = fma((double)Z[4 * v + i], (double)Z[4 * v + i], nn);
+            const ct_pair64 h = ct_swap32(nn, nn);
+            nn = h.a + h.b;
+            const auto lo = __builtin_amdgcn_permlane16_swap(ct_lo(nn), ct_lo(nn), false, false);
+            const auto hi = __builtin_amdgcn_permlane16_swap(ct_hi(nn), ct_hi(nn), false, false);
+            const double inv = c < rank[v] ? ct_rsq(ct_join(lo[0], hi[0]) + ct_join(lo[1], hi[1])) : 0.0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Z[4 * v + i] = (float)((double)Z[4 * v + i] * inv);
+        }
+    }
     // ---- 6. R = L^T X, stores --------------------------------------------------------------
     ct_lds_fence();
 #pragma unroll

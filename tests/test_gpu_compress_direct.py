@@ -243,3 +243,29 @@ def test_projection_holds_all_bits_of_l(P, points):
     for w in (0, 1):
         R = blk[:, w, P:] * np.where(blk[:, w, P:P + 1] * want[:, :1] < 0, -1, 1)   # the sign of the vector is free
         assert np.array_equal(R, want), (w, np.argwhere(R != want)[:4])
+
+
+@pytest.mark.parametrize("P,r,planted,bound", [(16, 9, 16, 6e-7), (16, 12, 6, 1.9e-5), (32, 16, 24, 5e-7), (32, 28, 16, 1.25e-5),
+                                               (64, 16, 24, 1.9e-6), (64, 24, 24, 2.95e-7), (64, 32, 24, 1.35e-5)])
+def test_fp32_factors_as_near_the_optimum_as_jacobi(P, r, planted, bound):
+    """fp32 factors of bf16 pages, at ranks inside the planted spectrum and in the noise
+    past it: L R departs from the best rank-r product by no more, on average, than with
+    one-sided Jacobi on every page (`bound`, its mean over six other draws of such pages)."""
+    import torch
+    import paper_2608_23843_amd as pk
+    n, d = 256, 128
+    rng = np.random.default_rng(100 * P + r)
+    X = rng.standard_normal((2, n, P, planted)) @ rng.standard_normal((2, n, planted, d)) + 0.05 * rng.standard_normal((2, n, P, d))
+    X = storage_round(X, "bf16")
+    k, v = (torch.from_numpy(x).to("cuda", torch.bfloat16).reshape(1, 1, n * P, d).contiguous() for x in X)
+    cache = pk.PuzzleKVCache(1, 1, 1, 1, d, P, n, r, 0, 0, "bf16", "f32")
+    cache.prefill(0, k, v, [n * P], default_rank=(r, r))
+    assert cache.device_status() == 0
+    blk = cache.export_pages(0, [0] * n, [0] * n, list(range(n))).cpu().double()[:, :2 * (P + d) * r]
+    for w, o in ((0, 0), (1, (P + d) * r)):
+        L, R = blk[:, o:o + P * r].reshape(n, P, r), blk[:, o + P * r:o + (P + d) * r].reshape(n, r, d)
+        U, s, Vh = torch.linalg.svd(torch.from_numpy(X[w]).double(), full_matrices=False)
+        best = (U[:, :, :r] * s[:, None, :r]) @ Vh[:, :r]
+        dep = (L @ R - best).flatten(1).norm(dim=1) / best.flatten(1).norm(dim=1)
+        assert float(dep.mean()) <= bound, (w, float(dep.mean()))
+        assert float((L.transpose(1, 2) @ L - torch.eye(r, dtype=torch.float64)).abs().max()) <= 1e-6
