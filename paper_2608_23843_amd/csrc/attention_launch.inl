@@ -48,7 +48,11 @@ static int attention_sched(const Geo &g, int pages_per_chunk) {
     //   block claims 46.3 -> 42.4 us; the batch-1 32K layer (per-wave claims)
     //   loses (27.9 -> 29.3 us), where the static first round gives the dense
     //   pages to a few waves.
-    const bool short_stream = pages_per_chunk <= 8 * kMfmaWaves;
+    //   Pre-RoPE streams (wave claims at any length) gain from four pages per
+    //   wave on: 2 sequences of 65,501 tokens (eight) 68.5 -> 67.7 us, of
+    //   49,152 50.1 -> 49.6, of 32,768 (four) 39.8 -> 39.4; of 24,576 (three)
+    //   34.7 -> 35.3, of 12,288 27.3 -> 28.7.
+    const bool short_stream = pages_per_chunk <= 3 * kMfmaWaves;
     const bool wave_claims = g.key_t || (g.P == 64 && pages_per_chunk <= 2 * kMfmaWaves);
     return (wave_claims ? kSchedWaveClaims : 0) | (short_stream && wave_claims ? 0 : kSchedReverse);
 }
