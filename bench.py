@@ -36,7 +36,7 @@ HBM_PEAK_GBPS = 8000.0
 EVENT_STRIDE = 8   # decode steps: the attention call of every EVENT_STRIDE-th layer is timed with events
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2608_23843_amd", "csrc", f)
                   for f in ("attention.inl", "attention_mfma.inl", "attention_q4.inl", "attention_launch.inl",
-                            "global_svd.inl")]
+                            "attention_plan.h", "global_svd.inl")]
 
 
 def log(msg: str) -> None:

@@ -464,8 +464,8 @@ pkv_status pkv_device_status(pkv_stream s, uint32_t *bits);
  * sweeps that decompositions on the current device have executed since the
  * last call, summed over decompositions (a page's K and V count as two).
  * bf16 pages are decomposed directly, without sweeps, except those whose
- * spectrum has eigenvalues too close to separate; fp32 pages always take
- * sweeps. The factors do not depend on it. */
+ * spectrum has eigenvalues too close to separate and 64-token pages of ranks
+ * above 32; fp32 pages always take sweeps. The factors do not depend on it. */
 pkv_status pkv_compress_sweeps(pkv_stream s, uint64_t *sweeps);
 /* Message of the last error on this thread ("" if none). */
 const char *pkv_last_error(void);

@@ -321,9 +321,15 @@ __device__ void publish_and_merge(const Geo &g, int64_t head, const Partials &pp
 // so what bounds a short cache is the launch, those waits and the merge, a
 // long one its loads. The tile loops over ranks stay loops, with Z and Y passed
 // through LDS: the code runs from a cold instruction cache, and unrolled over
-// four rank tiles it took longer than the loads. A workgroup of 256 threads sharing one page through LDS,
-// with one entry per load and a barrier per phase, took 71 us on a 4K fp32
-// cache of 8 KV heads (21 MB) against 17 us.
+// four rank tiles it took longer than the loads. A workgroup of 256 threads
+// sharing one page through LDS, with one entry per load, a barrier per phase and
+// 1,024 workgroups, took 66 us on a 4K fp32 cache of 8 KV heads (21 MB) against
+// 16; at 32K 342 against 41, at 128K 956 against 165 (605 MB), with d = 256 and
+// rank 48 at 32K 707 against 129 (504 MB), d = 192 at 4K 69 against 34, and on
+// bf16 pages of rank 64 at 128K 2,047 against 276 (805 MB). With 512 or 1,024
+// workgroups this kernel loses at all of these (4K 25 and 36 us, 128K 175 and
+// 202, d = 256 150 and 211): the merge grows and a head's waves share less.
+// 16-token pages of 64 dims alone gain from 512 (32K: 45 -> 38 us).
 
 constexpr int kGenWaves = 8, kGenThreads = 64 * kGenWaves;
 

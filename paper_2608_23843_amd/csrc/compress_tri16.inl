@@ -11,7 +11,7 @@
 // What bounds it: vector-ALU issue and, with one page's work so short, the
 // page reads of the first and last phase. Measured against Jacobi in fp32
 // vector code (k_compress): a 16K prompt of 8 KV heads at (r_K, r_V) = (9, 9)
-// 510 -> 68 us.
+// 510 -> 69 us.
 // Included by pkv_kernels.hip after compress_tri.inl.
 
 namespace pkv {
