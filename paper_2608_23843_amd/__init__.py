@@ -13,7 +13,7 @@ import ctypes
 import numpy as np
 
 from . import _lib
-from ._lib import (PKV_BF16, PKV_DENSE, PKV_EMPTY, PKV_F32, PKV_FACTOR, PKV_GLOBAL, PKV_INT4, PKV_OP_ATTENTION,
+from ._lib import (PKV_BF16, PKV_DENSE, PKV_E_WORKSPACE, PKV_EMPTY, PKV_F32, PKV_FACTOR, PKV_GLOBAL, PKV_INT4, PKV_OP_ATTENTION,
                    PKV_OP_COMPRESS, PKV_OP_GLOBAL_ATTENTION, PKV_OP_GLOBAL_PREFILL, PKV_OP_IMPORT, PKV_OP_PREFILL,
                    PuzzleKVError, check)
 
@@ -214,14 +214,16 @@ class PuzzleKVCache:
             out = torch.empty((c.batch, c.n_q_heads, c.head_dim), dtype=torch.float32, device=self.device)
         if lse is None:
             lse = torch.empty((c.batch, c.n_q_heads), dtype=torch.float32, device=self.device)
-        need = self.workspace_bytes(PKV_OP_ATTENTION, int(seq.max()) if seq.size else 0)
-        if workspace is None or workspace.numel() < need:
-            # zero-filled on first use (the merge counters live in it)
-            workspace = torch.zeros(max(need, 1), dtype=torch.uint8, device=self.device)
-        check(self.lib.pkv_mixed_decode_attention(ctypes.byref(c), layer, q.data_ptr(), _np_ptr(seq),
-                                                  out.data_ptr(), lse.data_ptr(), workspace.data_ptr(),
-                                                  workspace.numel(), _stream_handle(torch, stream)),
-              "pkv_mixed_decode_attention")
+        def call(ws):
+            return self.lib.pkv_mixed_decode_attention(ctypes.byref(c), layer, q.data_ptr(), _np_ptr(seq),
+                                                       out.data_ptr(), lse.data_ptr(), ws.data_ptr(), ws.numel(),
+                                                       _stream_handle(torch, stream))
+        status = PKV_E_WORKSPACE if workspace is None else call(workspace)
+        if status == PKV_E_WORKSPACE:
+            # none given, or too small: one zero-filled (the merge counters live in it)
+            need = self.workspace_bytes(PKV_OP_ATTENTION, int(seq.max()) if seq.size else 0)
+            status = call(torch.zeros(max(need, 1), dtype=torch.uint8, device=self.device))
+        check(status, "pkv_mixed_decode_attention")
         return out, lse
 
     def attention_noalloc(self, layer, q, seq_len, out, lse=None, stream=None):

@@ -421,9 +421,18 @@ pkv_status pkv_mixed_decode_attention(const pkv_cache *c, int32_t layer, const v
         max_T = std::max<int64_t>(max_T, seq_len[b]);
     }
     LaunchCtx L = ctx(c, layer, s);
-    size_t need = (size_t)attention_call_bytes(L.geo, max_T);
-    if ((st = check_ws(ws, ws_bytes, need)) != PKV_OK) return st;
+    const size_t need = (size_t)attention_call_bytes(L.geo, max_T);
     AttnPlan plan = attention_plan(L.geo, max_T);
+    bool fits = ws_bytes >= need;
+    if (ws && !fits) {
+        // the number of chunks is not monotone in the length, so a workspace
+        // sized for a longer sequence can be smaller: that length's plan then
+        for (int64_t n = ceil_div(max_T, L.geo.P) + 1; n <= c->max_pages && !fits; ++n)
+            if ((fits = ws_bytes >= (size_t)attention_call_bytes(L.geo, n * L.geo.P)))
+                plan = attention_plan(L.geo, n * L.geo.P);
+    }
+    if (!ws || !fits)
+        if ((st = check_ws(ws, ws_bytes, need)) != PKV_OK) return st;
     return check_launch(launch_attention(L, plan, q, seq, out, lse, ws), "pkv_mixed_decode_attention");
 }
 

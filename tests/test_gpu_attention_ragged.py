@@ -7,6 +7,33 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("Hkv,B,P,d,dtype,factors,longest,lens", [
+    (8, 1, 64, 128, "bf16", "bf16", 33 * 64, [[32 * 64], [31 * 64 + 5], [33 * 64]]),
+    (8, 1, 64, 128, "bf16", "int4", 33 * 64, [[32 * 64]]),
+    (4, 2, 64, 128, "bf16", "bf16", 33 * 64, [[32 * 64, 70], [64, 31 * 64], [2000, 2001]]),
+    (4, 1, 16, 96, "f32", "f32", 65 * 16, [[64 * 16], [1]])])
+def test_workspace_for_a_longer_length_serves_shorter_ones(Hkv, B, P, d, dtype, factors, longest, lens, monkeypatch):
+    """A shorter call may split its heads further than the longest and so ask for more
+    partial states; it takes a plan that fits the workspace it is given."""
+    import torch
+    import paper_2608_23843_amd as pk
+    r, G = 8, 2
+    g = torch.Generator(device="cuda").manual_seed(longest)
+    cache = pk.PuzzleKVCache(1, B, Hkv, Hkv * G, d, P, -(-longest // P), r, P, 2 * P, dtype, factors)
+    k, v = (torch.randn(B, Hkv, longest, d, generator=g, device="cuda").to(cache.qdtype) for _ in range(2))
+    q = torch.randn(B, Hkv * G, d, generator=g, device="cuda").to(cache.qdtype)
+    ws = cache.workspace(pk.PKV_OP_ATTENTION, longest)
+    tol = 5e-4 if factors == "int4" else 1e-5   # the order of the fp32 sums
+    for n in lens:
+        cache.prefill(0, k, v, n, default_rank=(r, r))
+        ro, rl = cache.attention(0, q, n)
+        with monkeypatch.context() as m:
+            m.setattr(torch, "zeros", None)   # the binding makes no workspace of its own
+            o, l = cache.attention(0, q, n, workspace=ws)
+        assert (o - ro).norm() <= tol * ro.norm() and (l - rl).abs().max() <= tol * float(rl.abs().max())
+        assert cache.device_status() == 0
+
+
 @pytest.mark.parametrize("Hkv,G,P,d,dtype,factors,lens", [
     (1, 8, 64, 128, "bf16", "bf16", [20011, 1, 0, 4097, 64, 9000]),                 # many chunks against one
     (8, 4, 64, 128, "bf16", "bf16", [6001] + [65 + 97 * i for i in range(24)]),      # more heads than CUs would hold
